@@ -1,6 +1,6 @@
 """The deposit and the kick keep to their LDS window wherever the particles and
 the box allow it: on boxes narrower than the window, whose cells it holds more
-than once.  What leaves it still gives the right sums (the other tests), but
+than once, and with masses too far apart for fixed point.  What leaves it still gives the right sums (the other tests), but
 takes eight adds to memory a particle instead of one a cell and chunk, ten times
 the time and more; the bounds of 4 lie between."""
 import numpy as np
@@ -40,6 +40,15 @@ def test_narrow_boxes_keep_to_the_window(shape, wide):
     x = np.random.default_rng(71).uniform(0.0, 1.0, (3, N))
     m = np.full(N, 1.0 / N)
     assert _ms(shape, x, m) <= 4.0 * _ms(wide, x, m)
+
+
+@pytest.mark.parametrize("width", [1.0, 0.02])
+def test_masses_far_apart_keep_to_the_window(width):
+    rng = np.random.default_rng(73)
+    x = 0.5 + width * rng.uniform(-0.5, 0.5, (3, N))
+    m = np.full(N, 1.0 / N)
+    apart = m * 10.0 ** rng.uniform(-9.0, 0.0, N)
+    assert _ms((32, 32, 32), x, apart) <= 4.0 * _ms((32, 32, 32), x, m)
 
 
 @pytest.mark.parametrize("shape", [(8, 8, 8), (4, 16, 8), (1, 2, 16), (32, 8, 2), (16, 1, 4)])
