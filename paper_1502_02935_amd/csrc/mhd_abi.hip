@@ -726,13 +726,14 @@ int upload_gelu_table(mhd_ctx* c) {
     o[1] = (float)(a1 - 2.0 * o[2] * xc);
     o[0] = i == 0 ? 0.0f : (float)(a0 - o[1] * xc - o[2] * xc * xc);
   }
-  // beyond the table: 0 and x (the smallest c2 keeps an infinite x infinite
-  // and is lost on any other below 1e30)
+  // beyond the table: 0 for every finite x (an infinite one gives NaN), and x:
+  // there the smallest c2 keeps an infinite x infinite, and it is at most 5e-7
+  // of any other
   float* lo = &h[4 * (size_t)(kGeluN / 2)];
   float* hi = &h[4 * (size_t)(kGeluN / 2 - 1)];
-  lo[0] = lo[1] = hi[0] = 0.0f;
+  lo[0] = lo[1] = lo[2] = hi[0] = 0.0f;
   hi[1] = 1.0f;
-  lo[2] = -FLT_MIN, hi[2] = FLT_MIN;
+  hi[2] = FLT_TRUE_MIN;
   if (hipMemcpyAsync(c->ws + c->L.off_gelu, h.data(), h.size() * sizeof(float),
                      hipMemcpyHostToDevice, c->st) != hipSuccess ||
       hipStreamSynchronize(c->st) != hipSuccess)

@@ -392,8 +392,8 @@ constexpr int kMlpFragBytes = 14 * 64 * 16;
 // (-kGeluN / 2 <= i < kGeluN / 2, at entry i mod kGeluN) for the arguments that
 // round, in quarters of h, to 4 i .. 4 i + 3 -- from (i - 1/8) h to (i + 7/8) h,
 // together [-6, 6) --, each c0 + x (c1 + x c2) as 4 floats (c0, c1, c2, 0); the
-// lowest is 0 and the highest x, for every argument beyond.  Written by the
-// host at initialisation.
+// lowest is 0 and the highest x, for every argument beyond (infinities: NaN and
+// infinity).  Written by the host at initialisation.
 constexpr int kGeluN = 512;
 constexpr float kGeluScale = kGeluN / 12.0f;
 constexpr float kGeluMagic = 12582912.0f;  // 1.5 x 2^23: the mantissa's last bit counts 1
