@@ -30,6 +30,8 @@
 // the x-lines' LDS slots are spread over the banks (-> 65 and 232 us).
 #include <math.h>
 
+#include <type_traits>
+
 #include "mhd_kernels.hpp"
 
 namespace mhd {
@@ -39,9 +41,24 @@ struct Cplx {
   T re, im;
 };
 
-template <class T>
-__device__ __forceinline__ Cplx<T> cmul(Cplx<T> a, Cplx<T> b) {
-  return Cplx<T>{a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
+// Arithmetic of the z-lines and of the y- and x-lines on the way back: FP32 ones
+// are transformed in FP64 registers (what they read, keep in LDS and write is
+// FP32).  Half spectra and paired rows round each value once where a full complex
+// array rounded it and its mirror image apart: all in FP32, the error of grad Psi
+// was 3.0 to 3.7 times that of rounding Psi itself (32^3 to 256^3; a full array
+// 3.0 to 3.4), and 1.7 to 2.3 so.  A step with two solves 467 -> 474 us at 128^3,
+// 2972 -> 3010 at 256^3 (the x-lines forward too: no smaller error, 477 and
+// 3018).
+using Fine = double;
+
+template <class A, class T>
+__device__ __forceinline__ Cplx<A> cast(Cplx<T> v) {
+  return Cplx<A>{(A)v.re, (A)v.im};
+}
+template <class A, class T>
+__device__ __forceinline__ Cplx<A> cmul(Cplx<A> a, Cplx<T> w) {
+  const Cplx<A> b = cast<A>(w);
+  return Cplx<A>{a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
 }
 
 // Row l = j + ny k of the box: the padded index of its first cell (ny is a
@@ -126,6 +143,7 @@ __device__ __forceinline__ Cplx<T> twiddle(const Cplx<T>* __restrict__ tw, int q
 }
 
 // The two halves of a line's DFT of N = R1 R2 points in LDS (L).
+// Both in arithmetic of type A, on values of type T.
 // first: for one n2 < R2 the R1-point DFT over x[R2 n1 + n2] (a[n1]), times
 // W_N^(n2 k1) (w, loaded before the values), to the slots R2 k1 + n2.
 // second: for one k1 < R1 the R2-point DFT over the R2 contiguous values, left
@@ -137,27 +155,27 @@ __device__ __forceinline__ void load_twiddles(Cplx<T> w[R1], int n2,
 #pragma unroll
   for (int k1 = 1; k1 < R1; ++k1) w[k1] = twiddle<T, N, SIGN>(tw, (n2 * k1) & (N - 1));
 }
-template <class T, int R1, int R2, int SIGN, int S = R2>
-__device__ __forceinline__ void dft_first(Cplx<T>* L, int n2, Cplx<T> a[R1],
+template <class A, class T, int R1, int R2, int SIGN, int S = R2>
+__device__ __forceinline__ void dft_first(Cplx<T>* L, int n2, Cplx<A> a[R1],
                                           const Cplx<T> w[R1]) {
-  dft_reg<T, R1, SIGN>(a);
-  L[n2] = a[0];
+  dft_reg<A, R1, SIGN>(a);
+  L[n2] = cast<T>(a[0]);
 #pragma unroll
-  for (int k1 = 1; k1 < R1; ++k1) L[S * k1 + n2] = cmul(a[k1], w[k1]);
+  for (int k1 = 1; k1 < R1; ++k1) L[S * k1 + n2] = cast<T>(cmul(a[k1], w[k1]));
 }
 // x-lines: from the line in LDS, in place.
-template <class T, int R1, int R2, int SIGN, int S>
+template <class A, class T, int R1, int R2, int SIGN, int S>
 __device__ __forceinline__ void dft_first_lds(Cplx<T>* L, int n2, const Cplx<T> w[R1]) {
-  Cplx<T> a[R1];
+  Cplx<A> a[R1];
 #pragma unroll
-  for (int n1 = 0; n1 < R1; ++n1) a[n1] = L[S * n1 + n2];
-  dft_first<T, R1, R2, SIGN, S>(L, n2, a, w);
+  for (int n1 = 0; n1 < R1; ++n1) a[n1] = cast<A>(L[S * n1 + n2]);
+  dft_first<A, T, R1, R2, SIGN, S>(L, n2, a, w);
 }
-template <class T, int R1, int R2, int SIGN, int S = R2>
-__device__ __forceinline__ void dft_second(const Cplx<T>* L, int k1, Cplx<T> a[R2]) {
+template <class A, class T, int R1, int R2, int SIGN, int S = R2>
+__device__ __forceinline__ void dft_second(const Cplx<T>* L, int k1, Cplx<A> a[R2]) {
 #pragma unroll
-  for (int n2 = 0; n2 < R2; ++n2) a[n2] = L[S * k1 + n2];
-  dft_reg<T, R2, SIGN>(a);
+  for (int n2 = 0; n2 < R2; ++n2) a[n2] = cast<A>(L[S * k1 + n2]);
+  dft_reg<A, R2, SIGN>(a);
 }
 
 // x-lines.  A line pair holds rows 2m and 2m + 1 (of ny nz rows) as real and
@@ -220,13 +238,13 @@ __global__ void __launch_bounds__(kFftXThreads) k_fft_x(Geo g, const T* __restri
   }
   __syncthreads();
   for (int t = threadIdx.x; t < np * R2; t += kFftXThreads)  // one n2: R2 divides the step
-    dft_first_lds<T, R1, R2, -1, R2 + 1>(buf + (t / R2) * LS, n2, w);
+    dft_first_lds<T, T, R1, R2, -1, R2 + 1>(buf + (t / R2) * LS, n2, w);
   __syncthreads();
   for (int t = threadIdx.x; t < np * R1; t += kFftXThreads) {
     Cplx<T>* L = buf + (t / R1) * LS;
     const int k1 = t % R1;
     Cplx<T> a[R2];
-    dft_second<T, R1, R2, -1, R2 + 1>(L, k1, a);
+    dft_second<T, T, R1, R2, -1, R2 + 1>(L, k1, a);
 #pragma unroll
     for (int k2 = 0; k2 < R2; ++k2) L[(R2 + 1) * k1 + k2] = a[k2];
   }
@@ -282,15 +300,15 @@ __global__ void __launch_bounds__(kFftXThreads) k_fft_x_back(Geo g, const Cplx<T
   }
   __syncthreads();
   for (int t = threadIdx.x; t < np * R2; t += kFftXThreads)  // one n2: R2 divides the step
-    dft_first_lds<T, R1, R2, +1, R2 + 1>(buf + (t / R2) * LS, n2, w);
+    dft_first_lds<Fine, T, R1, R2, +1, R2 + 1>(buf + (t / R2) * LS, n2, w);
   __syncthreads();
   for (int t = threadIdx.x; t < np * R1; t += kFftXThreads) {
     Cplx<T>* L = buf + (t / R1) * LS;
     const int k1 = t % R1;
-    Cplx<T> a[R2];
-    dft_second<T, R1, R2, +1, R2 + 1>(L, k1, a);
+    Cplx<Fine> a[R2];
+    dft_second<Fine, T, R1, R2, +1, R2 + 1>(L, k1, a);
 #pragma unroll
-    for (int k2 = 0; k2 < R2; ++k2) L[(R2 + 1) * k1 + k2] = a[k2];
+    for (int k2 = 0; k2 < R2; ++k2) L[(R2 + 1) * k1 + k2] = cast<T>(a[k2]);
   }
   __syncthreads();
   for (int t = threadIdx.x; t < np * 2 * N; t += kFftXThreads) {
@@ -327,14 +345,17 @@ constexpr int line_threads() {
 // The first half of a line at base (element stride st) straight from memory:
 // thread e0 < R2 of the line's G takes n2 = e0, whose elements are the ones it
 // would stage for the others anyway.
-template <class T, int R1, int R2, int SIGN>
+template <class A, class T, int R1, int R2, int SIGN>
 __device__ __forceinline__ void first_from(Cplx<T>* L, const Cplx<T>* base, int st, int e0,
                                            const Cplx<T>* __restrict__ tw) {
-  Cplx<T> a[R1], w[R1];
+  Cplx<T> v[R1], w[R1];
   load_twiddles<T, R1, R2, SIGN>(w, e0, tw);
 #pragma unroll
-  for (int n1 = 0; n1 < R1; ++n1) a[n1] = base[(size_t)(R2 * n1 + e0) * st];
-  dft_first<T, R1, R2, SIGN>(L, e0, a, w);
+  for (int n1 = 0; n1 < R1; ++n1) v[n1] = base[(size_t)(R2 * n1 + e0) * st];
+  Cplx<A> a[R1];
+#pragma unroll
+  for (int n1 = 0; n1 < R1; ++n1) a[n1] = cast<A>(v[n1]);
+  dft_first<A, T, R1, R2, SIGN>(L, e0, a, w);
 }
 
 template <class T, int R1, int R2, int SIGN>
@@ -344,6 +365,7 @@ __global__ void __launch_bounds__((line_threads<R1, R2>()))
   constexpr int NT = line_threads<R1, R2>(), G = NT / TL;
   static_assert(G >= R2, "a thread a first-half DFT");
   __shared__ Cplx<T> buf[TL * LS];
+  using A = std::conditional_t<(SIGN < 0), T, Fine>;
   const int H = g.n[0] / 2 + 1;
   const int line = threadIdx.x % TL, e0 = threadIdx.x / TL;
   const int l = xcd_block() * TL + line;  // x + H k
@@ -351,14 +373,14 @@ __global__ void __launch_bounds__((line_threads<R1, R2>()))
   const int k = l / H;
   Cplx<T>* base = c + (size_t)k * H * N + (l - k * H);
   Cplx<T>* L = buf + line * LS;
-  if (on && e0 < R2) first_from<T, R1, R2, SIGN>(L, base, H, e0, tw);
+  if (on && e0 < R2) first_from<A, T, R1, R2, SIGN>(L, base, H, e0, tw);
   __syncthreads();
   if (on)
     for (int k1 = e0; k1 < R1; k1 += G) {
-      Cplx<T> a[R2];
-      dft_second<T, R1, R2, SIGN>(L, k1, a);
+      Cplx<A> a[R2];
+      dft_second<A, T, R1, R2, SIGN>(L, k1, a);
 #pragma unroll
-      for (int k2 = 0; k2 < R2; ++k2) base[(size_t)(k1 + R1 * k2) * H] = a[k2];
+      for (int k2 = 0; k2 < R2; ++k2) base[(size_t)(k1 + R1 * k2) * H] = cast<T>(a[k2]);
     }
 }
 
@@ -400,7 +422,7 @@ __global__ void __launch_bounds__((line_threads<R1, R2>())) k_fft_z_solve(
         if (k2 > 0) wb[u][k2] = twiddle<T, N, +1>(tw, (k1 * k2) & (N - 1));
       }
     }
-    if (e0 < R2) first_from<T, R1, R2, -1>(L, base, plane, e0, tw);
+    if (e0 < R2) first_from<Fine, T, R1, R2, -1>(L, base, plane, e0, tw);
   }
   __syncthreads();
   if (on) {
@@ -408,25 +430,26 @@ __global__ void __launch_bounds__((line_threads<R1, R2>())) k_fft_z_solve(
     for (int u = 0; u < U; ++u) {
       const int k1 = e0 + G * u;
       if (k1 >= R1) break;
-      Cplx<T> a[R2];
-      dft_second<T, R1, R2, -1>(L, k1, a);
+      Cplx<Fine> a[R2];
+      dft_second<Fine, T, R1, R2, -1>(L, k1, a);
 #pragma unroll
-      for (int k2 = 0; k2 < R2; ++k2) a[k2] = Cplx<T>{a[k2].re * s[u][k2], a[k2].im * s[u][k2]};
-      dft_reg<T, R2, +1>(a);
-      L[R2 * k1] = a[0];
+      for (int k2 = 0; k2 < R2; ++k2)
+        a[k2] = Cplx<Fine>{a[k2].re * s[u][k2], a[k2].im * s[u][k2]};
+      dft_reg<Fine, R2, +1>(a);
+      L[R2 * k1] = cast<T>(a[0]);
 #pragma unroll
-      for (int m2 = 1; m2 < R2; ++m2) L[R2 * k1 + m2] = cmul(a[m2], wb[u][m2]);
+      for (int m2 = 1; m2 < R2; ++m2) L[R2 * k1 + m2] = cast<T>(cmul(a[m2], wb[u][m2]));
     }
   }
   __syncthreads();
   if (on)
     for (int m2 = e0; m2 < R2; m2 += G) {
-      Cplx<T> a[R1];
+      Cplx<Fine> a[R1];
 #pragma unroll
-      for (int k1 = 0; k1 < R1; ++k1) a[k1] = L[R2 * k1 + m2];
-      dft_reg<T, R1, +1>(a);
+      for (int k1 = 0; k1 < R1; ++k1) a[k1] = cast<Fine>(L[R2 * k1 + m2]);
+      dft_reg<Fine, R1, +1>(a);
 #pragma unroll
-      for (int m1 = 0; m1 < R1; ++m1) base[(size_t)(m2 + R2 * m1) * plane] = a[m1];
+      for (int m1 = 0; m1 < R1; ++m1) base[(size_t)(m2 + R2 * m1) * plane] = cast<T>(a[m1]);
     }
 }
 
