@@ -1393,6 +1393,9 @@ void launch_gather(const Geo& g, Cons<T> s, T* cell5, T* bx, T* by, T* bz, hipSt
 // (4 scalars, both launches, with 16 / 8 / 4 / 2 planes: 128^3 119 / 91 / 99 /
 // 96 us, 70x60x50 77 / 46 / 30 / 25, 256^3 569 / 562 / 543 / 633).
 //
+// Boxes that would leave most of a tile empty take one cell a thread after all
+// (k_scalar_cells).
+//
 // Along a periodic axis every neighbour is read at its interior image, so
 // a fully periodic step needs no ghost values of the scalars, the density
 // or the mass fluxes.
@@ -1518,10 +1521,69 @@ __global__ void __launch_bounds__(kSwX* kSwY) k_scalar_update(Geo g, int ntx, in
   }
 }
 
+// The same, one cell a thread with its whole stencil loaded, for boxes whose
+// tiles would be mostly empty; every load before the first store.
+template <class T, int NS, bool FO>
+__global__ void __launch_bounds__(kSpanThreads) k_scalar_cells(Geo g, Span sp,
+                                                               const T* __restrict__ rho,
+                                                               Flux<T> f, Scal<T> x0, Scal<T> xs,
+                                                               Scal<T> x1, Muscl<T> mu,
+                                                               DtRef dtr) {
+  constexpr int H = FO ? 1 : 2, W = 2 * H + 1;
+  const Pt pt = span_point(g, sp);
+  if (!pt.valid) return;
+  const int p = pt.p, c[3] = {pt.i, pt.j, pt.k};
+  const double dt = (dtr.ptr ? *dtr.ptr : dtr.value) * dtr.factor;
+  T w[NS][3][W], v[NS], lo[3], hi[3], r[3];
+  const T ic = rcp(rho[p]);
+#pragma unroll
+  for (int m = 0; m < NS; ++m) {
+    v[m] = x0.x[m][p];
+    w[m][0][H] = xs.x[m][p] * ic;
+  }
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    lo[a] = f.f[a][0][p], hi[a] = f.f[a][0][upper_face(g, a, c[a], p)];
+    r[a] = (T)(dt / g.d[a]);
+#pragma unroll
+    for (int s = 0; s < W; ++s) {
+      const int q = p + (int)axis_step(g, a, c[a], s - H) * stride_of(g, a);
+      const T ir = s == H ? ic : rcp(rho[q]);
+#pragma unroll
+      for (int m = 0; m < NS; ++m) w[m][a][s] = s == H ? w[m][0][H] : xs.x[m][q] * ir;
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < NS; ++m)
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      v[m] -= r[a] * (scalar_face<T, FO>(mu, hi[a], w[m][a] + 1) -
+                      scalar_face<T, FO>(mu, lo[a], w[m][a]));
+#pragma unroll
+  for (int m = 0; m < NS; ++m) x1.x[m][p] = v[m];
+}
+
+// A tile costs what its 512 threads do, however many of them hold a cell.  us a
+// step, cells / tiles, one and eight scalars in FP32 and one in FP64, by the
+// share of the threads that do: 3 % (2x256x256) 22 / 58, 50 / 149, 30 / 96; 25 %
+// (16x256x128) 25 / 38, 67 / 86, 39 / 78; 50 % (32x128x128) 23 / 26, 69 / 56,
+// 34 / 41; 65 % (130x130x66) 31 / 40, 124 / 106, 62 / 93; 75 % (100^3) 34 / 31,
+// 111 / 85, 64 / 51.
 template <class T, int NS>
 static void scalar_update_ns(const Geo& g, const T* rho, Flux<T> f, Scal<T> x0, Scal<T> xs,
                              Scal<T> x1, Muscl<T> m, DtRef dt, hipStream_t st) {
   const int ntx = (g.n[0] + kSwX - 1) / kSwX, nty = (g.n[1] + kSwY - 1) / kSwY;
+  const double used = (double)g.n[0] * g.n[1] / ((double)ntx * kSwX * nty * kSwY);
+  if (used < (sizeof(T) == 8 || NS == 1 ? 0.7 : 0.4)) {
+    const Span sp = make_span(g, 0, g.n[0] - 1, 0, g.n[1] - 1, 0, g.n[2] - 1);
+    if (m.first_order)
+      hipLaunchKernelGGL((k_scalar_cells<T, NS, true>), span_grid(sp), dim3(kSpanThreads), 0, st,
+                         g, sp, rho, f, x0, xs, x1, m, dt);
+    else
+      hipLaunchKernelGGL((k_scalar_cells<T, NS, false>), span_grid(sp), dim3(kSpanThreads), 0, st,
+                         g, sp, rho, f, x0, xs, x1, m, dt);
+    return;
+  }
   const int nblk = ntx * nty * ((g.n[2] + g.swz - 1) / g.swz);
   if (m.first_order)
     hipLaunchKernelGGL((k_scalar_update<T, NS, true>), dim3((unsigned)nblk), dim3(kSwX * kSwY), 0,
