@@ -176,6 +176,20 @@ struct Scal {
 // are tile t's particles.
 constexpr int kTile = 8;
 constexpr int kChunk = 2048;  // particles per block of the deposit and the kick
+// Chunks of a tile's c particles, and their records (tile, first, end) appended to
+// the list from entry k on; returns the next entry.  Indices run up to the
+// largest int, so nothing is formed beyond a tile's end.
+__host__ __device__ constexpr int chunk_count(int c) { return c / kChunk + (c % kChunk != 0); }
+__host__ __device__ inline int list_chunks(int* chunk, int k, int t, int first, int c) {
+  for (int done = 0; done < c; ++k) {
+    const int n = c - done < kChunk ? c - done : kChunk;
+    chunk[1 + 3 * k] = t;
+    chunk[2 + 3 * k] = first + done;
+    done += n;
+    chunk[3 + 3 * k] = first + done;
+  }
+  return k;
+}
 template <class T>
 struct Parts {
   T* x;

@@ -196,7 +196,7 @@ __global__ void __launch_bounds__(1024) k_tile_scan(int* cnt, int* off, int* cur
   int s = 0, nc = 0;
   for (int t = lo; t < hi; ++t) {
     s += cnt[t];
-    nc += (cnt[t] + kChunk - 1) / kChunk;
+    nc += chunk_count(cnt[t]);
   }
   part[threadIdx.x] = s;
   cpart[threadIdx.x] = nc;
@@ -211,16 +211,12 @@ __global__ void __launch_bounds__(1024) k_tile_scan(int* cnt, int* off, int* cur
   }
   int base = part[threadIdx.x] - s, k = cpart[threadIdx.x] - nc;
   for (int t = lo; t < hi; ++t) {
-    const int c = cnt[t], end = base + c;
+    const int c = cnt[t];
     off[t] = base;
     cur[t] = base;
     cnt[t] = 0;
-    for (int q = base; q < end; q += kChunk, ++k) {
-      chunk[1 + 3 * k] = t;
-      chunk[2 + 3 * k] = q;
-      chunk[3 + 3 * k] = min(q + kChunk, end);
-    }
-    base = end;
+    k = list_chunks(chunk, k, t, base, c);
+    base += c;
   }
   if (threadIdx.x == 1023) {
     off[ntiles] = part[1023];
@@ -334,14 +330,13 @@ __device__ __forceinline__ float window_value(const unsigned long long* a, doubl
   return unit != 0.0 ? (float)((double)(long long)*a * unit) : *(const float*)a;
 }
 
-// Exponent e with |m| idv < 2^e for every mass m of particles q0 .. q1 - 1,
+// Exponent e with |m| idv < 2^e for every mass m of the nq particles at m,
 // or INT_MIN if the chunk cannot use fixed point.
-__device__ __forceinline__ int chunk_exponent(const float* __restrict__ m, int q0, int q1,
-                                              float idv) {
+__device__ __forceinline__ int chunk_exponent(const float* __restrict__ m, int nq, float idv) {
   __shared__ float hi[kPartThreads / 64], lo[kPartThreads / 64];
   float a = 0.f, b = INFINITY;
-  for (int q = q0 + (int)threadIdx.x; q < q1; q += kPartThreads) {
-    const float v = fabsf(m[q]) * idv;
+  for (int u = (int)threadIdx.x; u < nq; u += kPartThreads) {
+    const float v = fabsf(m[u]) * idv;
     a = v <= a || a != a ? a : v;  // a NaN stays
     if (v > 0.f) b = fminf(b, v);
   }
@@ -375,7 +370,8 @@ __global__ void __launch_bounds__(kPartThreads) k_deposit(Geo g, Parts<T> pp, Dt
   __shared__ typename DepositCell<T>::type acc[kWin3];
   if ((int)blockIdx.x >= pp.chunk[0]) return;
   const int t = pp.chunk[1 + 3 * blockIdx.x];
-  const int q0 = pp.chunk[2 + 3 * blockIdx.x], q1 = pp.chunk[3 + 3 * blockIdx.x];
+  // its particles q0 .. q0 + nq - 1, counted from q0: the end may be the largest int
+  const int q0 = pp.chunk[2 + 3 * blockIdx.x], nq = pp.chunk[3 + 3 * blockIdx.x] - q0;
   const int tx = t % pp.nt[0], ty = (t / pp.nt[0]) % pp.nt[1], tz = t / (pp.nt[0] * pp.nt[1]);
   const int o[3] = {tx * kTile, ty * kTile, tz * kTile};
   for (int i = threadIdx.x; i < kWin3; i += kPartThreads) acc[i] = 0;
@@ -384,14 +380,15 @@ __global__ void __launch_bounds__(kPartThreads) k_deposit(Geo g, Parts<T> pp, Dt
   const long long n = pp.n;
   double scale = 1.0, unit = 1.0;
   if constexpr (sizeof(T) == 4) {
-    const int e = __builtin_amdgcn_readfirstlane(chunk_exponent(pp.m, q0, q1, idv));
+    const int e = __builtin_amdgcn_readfirstlane(chunk_exponent(pp.m + q0, nq, idv));
     scale = e != INT_MIN ? ldexp(1.0, 50 - e) : 0.0;
     unit = e != INT_MIN ? ldexp(1.0, e - 50) : 0.0;
   }
   // a particle's values are loaded a turn ahead
   T px[3], pv[3], pm = T(0);
-  const auto fetch = [&](int q) {
-    if (q >= q1) return;
+  const auto fetch = [&](int u) {
+    if (u >= nq) return;
+    const int q = q0 + u;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       px[a] = pp.x[a * n + q];
@@ -399,14 +396,14 @@ __global__ void __launch_bounds__(kPartThreads) k_deposit(Geo g, Parts<T> pp, Dt
     }
     pm = pp.m[q];
   };
-  fetch(q0 + (int)threadIdx.x);
+  fetch((int)threadIdx.x);
   __syncthreads();
-  for (int q = q0 + (int)threadIdx.x; q < q1; q += kPartThreads) {
+  for (int u = (int)threadIdx.x; u < nq; u += kPartThreads) {
     int ci[3][2], wi[3];
     T w[3][2];
     bool in = true;
     const T cx[3] = {px[0], px[1], px[2]}, cv[3] = {pv[0], pv[1], pv[2]}, m = pm;
-    fetch(q + kPartThreads);
+    fetch(u + kPartThreads);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       T x = cx[a];
@@ -458,22 +455,24 @@ __global__ void __launch_bounds__(kPartThreads) k_kick_drift(Geo g, Parts<T> pp,
   __shared__ T gl[3][kWin3];
   if ((int)blockIdx.x >= pp.chunk[0]) return;
   const int t = pp.chunk[1 + 3 * blockIdx.x];
-  const int q0 = pp.chunk[2 + 3 * blockIdx.x], q1 = pp.chunk[3 + 3 * blockIdx.x];
+  // its particles q0 .. q0 + nq - 1, counted from q0: the end may be the largest int
+  const int q0 = pp.chunk[2 + 3 * blockIdx.x], nq = pp.chunk[3 + 3 * blockIdx.x] - q0;
   const int tx = t % pp.nt[0], ty = (t / pp.nt[0]) % pp.nt[1], tz = t / (pp.nt[0] * pp.nt[1]);
   const int o[3] = {tx * kTile, ty * kTile, tz * kTile};
-  const bool staged = q1 - q0 >= kStageMin;
+  const bool staged = nq >= kStageMin;
   const long long n = pp.n;
   // a particle's values are loaded a turn ahead, the first beside the window's
   T px[3], pv[3];
-  const auto fetch = [&](int q) {
-    if (q >= q1) return;
+  const auto fetch = [&](int u) {
+    if (u >= nq) return;
+    const int q = q0 + u;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       px[a] = pp.x[a * n + q];
       pv[a] = pp.v[a * n + q];
     }
   };
-  fetch(q0 + (int)threadIdx.x);
+  fetch((int)threadIdx.x);
   if (staged) {
     for (int i = threadIdx.x; i < kWin3; i += kPartThreads) {
       const int ai[3] = {i % kWin, (i / kWin) % kWin, i / (kWin * kWin)};
@@ -487,14 +486,15 @@ __global__ void __launch_bounds__(kPartThreads) k_kick_drift(Geo g, Parts<T> pp,
   __syncthreads();
   const double dt = (dtr.ptr ? *dtr.ptr : dtr.value) * dtr.factor;
   const T hdt = (T)(0.5 * dt), Tdt = (T)dt;
-  for (int q = q0 + (int)threadIdx.x; q < q1; q += kPartThreads) {
+  for (int u = (int)threadIdx.x; u < nq; u += kPartThreads) {
+    const int q = q0 + u;
     T xh[3], vh[3], w[3][2], acc[3] = {T(0), T(0), T(0)};
     int ci[3][2], wi[3];
     bool in = staged;
     const T cx[3] = {px[0], px[1], px[2]};
 #pragma unroll
     for (int a = 0; a < 3; ++a) vh[a] = pv[a];
-    fetch(q + kPartThreads);
+    fetch(u + kPartThreads);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       xh[a] = wrap_coord<T>(cx[a] + hdt * vh[a], g.x0[a], g.n[a] * g.d[a]);
