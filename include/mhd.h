@@ -262,7 +262,8 @@ int mhd_set_full_fluxes(mhd_ctx *ctx, int enable);
    compute neither the ghost layers of the cell arrays and primitives nor the
    fluxes outside the interior faces (their readers take the interior
    images); the copy's entries there are filled with the images' values.
-   Synchronises. */
+   Fluxes that a step does not keep (mhd_set_full_fluxes) read stale values;
+   of the x-faces, 1..4 then hold the sweep's own records.  Synchronises. */
 int mhd_debug_array(mhd_ctx *ctx, int what, void *d_out, size_t *n_out);
 
 /* Kernel classes timed by the profiling hook. */

@@ -185,7 +185,7 @@ Layout layout_of(const mhd_config* c) {
     const size_t np = (size_t)c->npart, nt = (size_t)ntiles_of(g);
     const size_t mc = np / kChunk + nt;  // chunks of at most kChunk particles per tile
     part = 2 * align_up(7 * np * es) + 2 * align_up(np * sizeof(int)) +
-           align_up((3 * nt + 1 + 1 + 3 * mc) * sizeof(int));
+           align_up((2 * nt + 1 + 3 * mc) * sizeof(int));
   }
   L.total = L.off_part + part;
   return L;
@@ -389,10 +389,9 @@ struct mhd_ctx {
       p.m = b + 6 * p.n;
       p.id = part_ids<T>(which);
       const int nt = ntiles_of(g);
-      // tile ints: counters [nt] (zero between sorts), offsets [nt + 1],
-      // cursors [nt], chunk list [1 + 3 max_chunks]
-      p.toff = tile_ints() + nt;
-      p.chunk = tile_ints() + 3 * nt + 1;
+      // tile ints: counters [nt] (zero between sorts), cursors [nt], chunk
+      // list [1 + 3 max_chunks]
+      p.chunk = tile_ints() + 2 * nt;
       for (int a = 0; a < 3; ++a) p.nt[a] = (g.n[a] + kTile - 1) / kTile;
       p.ntiles = nt;
       p.max_chunks = (int)(cfg.npart / kChunk + nt);
@@ -414,8 +413,7 @@ struct mhd_ctx {
       s.id = p.id;
       const int nt = ntiles_of(g);
       s.cnt = tile_ints();
-      s.off = s.cnt + nt;
-      s.cur = s.off + nt + 1;
+      s.cur = s.cnt + nt;
       s.chunk = s.cur + nt;
     }
     return s;

@@ -21,8 +21,9 @@
 // The passes are bound by memory and launch latency, so the steps that only
 // re-read the array are folded away: a full complex array with passes of
 // its own for the load and the division (nine launches) took 132 us a solve
-// at 128^3 FP32 and 620 us at 256^3; this form takes 65 and 232 us (256^3:
-// about 0.9 GB, 4 TB/s; 128^3: six launches of 6 to 13 us).  The in-register
+// at 128^3 FP32 and 620 us at 256^3; this form takes 68 and 251 us (256^3:
+// about 0.9 GB, 3.6 TB/s; 128^3: six launches of 6 to 14 us; 65 and 232 us with
+// all its arithmetic in FP32, see Fine).  The in-register
 // DFTs' factors are literals and the other twiddles are loaded ahead of the
 // values (with both read from the table where used: 96 and 374 us).  y- and
 // z-lines come from memory in the order their first half takes them, without

@@ -424,8 +424,8 @@ __device__ __forceinline__ int face_step(const Geo& g, int c, int d) {
 // face wrapped onto the interior images (the ghost layers are not filled),
 // each event counted as many times as the full range holds copies of the
 // face.
-// Blocks of 256 faces (128^3: 173 us a launch by event timing, 222 in blocks of
-// 640: the one barrier waits on every wave of the block).
+// Blocks of 256 faces (128^3: 172 us a launch, 222 in blocks of 640: the one
+// barrier waits on every wave of the block).
 constexpr int kMlpThreads = 256;
 
 template <class T, int A, bool LITE>
@@ -1388,7 +1388,7 @@ void launch_gather(const Geo& g, Cons<T> s, T* cell5, T* bx, T* by, T* bz, hipSt
 // sweep does: X of a column's planes k-2..k+2 stays in registers (one new
 // plane a step, divided by the density once), and the plane's tile with a
 // halo of two (first order: one) goes through LDS for the x- and
-// y-neighbours; 17 loads: 77 us (first order) and 98 us (MUSCL), and 421 ->
+// y-neighbours; 17 loads: 72 us (first order) and 103 us (MUSCL), and 421 ->
 // 285 us a launch at 256^3.  The flux sweep's chunk length serves here too
 // (4 scalars, both launches, with 16 / 8 / 4 / 2 planes: 128^3 119 / 91 / 99 /
 // 96 us, 70x60x50 77 / 46 / 30 / 25, 256^3 569 / 562 / 543 / 633).

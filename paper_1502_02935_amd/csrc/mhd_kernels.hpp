@@ -172,8 +172,7 @@ struct Scal {
 // N-body particles (context precision, structure of arrays): positions and
 // velocities [3][n] (x, y, z rows), masses [n], and each particle's index in
 // the caller's order; n = 0: none.  The library keeps them sorted by tile
-// (kTile^3 cells, the tile holding the particle's cell): toff[t] .. toff[t+1]
-// are tile t's particles.
+// (kTile^3 cells, the tile holding the particle's cell).
 constexpr int kTile = 8;
 constexpr int kChunk = 2048;  // particles per block of the deposit and the kick
 // Chunks of a tile's c particles, and their records (tile, first, end) appended to
@@ -197,7 +196,6 @@ struct Parts {
   T* m;
   int* id;
   long long n;
-  const int* toff;   // [ntiles + 1]
   const int* chunk;  // [1 + 3 max_chunks]: count, then (tile, first, end) per chunk
   int nt[3];         // tiles per axis
   int ntiles;
@@ -211,7 +209,6 @@ struct PartSort {
   T* m;
   int* id;
   int* cnt;    // [ntiles], zero between sorts
-  int* off;    // [ntiles + 1]
   int* cur;    // [ntiles]
   int* chunk;  // [1 + 3 max_chunks]
 };
@@ -324,11 +321,11 @@ void launch_scalar_update(const Geo& g, const T* rho, Flux<T> f, Scal<T> x0, Sca
                           Scal<T> x1, int ns, Muscl<T> m, DtRef dt, hipStream_t st);
 template <class T>
 void launch_scalar_ghosts(const Geo& g, Scal<T> x, int ns, hipStream_t st);
-// Interior [ns][nz][ny][nx] <-> padded scalar arrays.
 // Every point of the padded array a outside the interior takes its periodic
 // image's value (a fully periodic box).
 template <class T>
 void launch_wrap(const Geo& g, T* a, hipStream_t st);
+// Interior [ns][nz][ny][nx] <-> padded scalar arrays.
 template <class T>
 void launch_scalar_copy(const Geo& g, Scal<T> x, int ns, T* interior, bool in, hipStream_t st);
 // Psi of the stage density rho (padded primitive array) and its gradient
@@ -352,8 +349,7 @@ void launch_cfl_reduce(const Geo& g, const Physics& ph, double* part, int nb, Dt
 template <class T>
 void launch_particle_cfl(const Geo& g, Parts<T> pp, double* part, hipStream_t st);
 // Adds the cloud-in-cell density of the particles at x + h v (h = dt x
-// dt.factor, positions wrapped) to the real parts of the complex array c
-// ([nz][ny][nx] pairs).
+// dt.factor, positions wrapped) to the padded array c.
 template <class T>
 void launch_deposit(const Geo& g, Parts<T> pp, DtRef h, T* c, hipStream_t st);
 // Leapfrog with the potential gradient of gr (cell-centred, the corrector's):
@@ -365,7 +361,7 @@ void launch_kick_drift(const Geo& g, Parts<T> pp, Grav<T> gr, DtRef dt, hipStrea
 template <class T>
 void launch_particles_init(const Geo& g, Parts<T> pp, hipStream_t st);
 // Counting sort of pp by tile into the buffers of s (which then hold the
-// current order, with s.off the tile offsets).
+// current order) and the list of chunks.
 template <class T>
 void launch_particle_sort(const Geo& g, Parts<T> pp, PartSort<T> s, hipStream_t st);
 // Positions and velocities in the caller's order (x_out, v_out may be null);

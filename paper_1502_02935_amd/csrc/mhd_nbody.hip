@@ -183,13 +183,11 @@ __global__ void __launch_bounds__(kPartThreads) k_tile_count(Geo g, Parts<T> pp,
 }
 
 // One block, each thread a contiguous share of the tiles: the exclusive scan
-// of cnt into off (ntiles + 1 entries) and the scatter's cursors, cnt back to
-// zero for the next sort, and the list of chunks of at most kChunk particles
-// within each tile (count, then tile, first, end of each).  (As seven
+// of cnt into the scatter's cursors, cnt back to zero for the next sort, and the
+// list of chunks of at most kChunk particles within each tile (count, then tile, first, end of each).  (As seven
 // launches -- clear, count, scan, scatter, chunk counts, their scan, the list
 // -- the small ones took 25 us a sort.)
-__global__ void __launch_bounds__(1024) k_tile_scan(int* cnt, int* off, int* cur, int* chunk,
-                                                    int ntiles) {
+__global__ void __launch_bounds__(1024) k_tile_scan(int* cnt, int* cur, int* chunk, int ntiles) {
   __shared__ int part[1024], cpart[1024];
   const int share = (ntiles + 1023) / 1024;
   const int lo = min(ntiles, (int)threadIdx.x * share), hi = min(ntiles, lo + share);
@@ -212,16 +210,12 @@ __global__ void __launch_bounds__(1024) k_tile_scan(int* cnt, int* off, int* cur
   int base = part[threadIdx.x] - s, k = cpart[threadIdx.x] - nc;
   for (int t = lo; t < hi; ++t) {
     const int c = cnt[t];
-    off[t] = base;
     cur[t] = base;
     cnt[t] = 0;
     k = list_chunks(chunk, k, t, base, c);
     base += c;
   }
-  if (threadIdx.x == 1023) {
-    off[ntiles] = part[1023];
-    chunk[0] = cpart[1023];
-  }
+  if (threadIdx.x == 1023) chunk[0] = cpart[1023];
 }
 
 // Same blocks and table as the count: each distinct tile reserves its
@@ -280,8 +274,7 @@ void launch_particle_sort(const Geo& g, Parts<T> pp, PartSort<T> s, hipStream_t 
   if (pp.n <= 0) return;
   hipLaunchKernelGGL(k_tile_count<T>, dim3(sort_blocks(pp.n)), dim3(kPartThreads), 0, st, g, pp,
                      s.cnt);
-  hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(1024), 0, st, s.cnt, s.off, s.cur, s.chunk,
-                     pp.ntiles);
+  hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(1024), 0, st, s.cnt, s.cur, s.chunk, pp.ntiles);
   hipLaunchKernelGGL(k_tile_scatter<T>, dim3(sort_blocks(pp.n)), dim3(kPartThreads), 0, st, g,
                      pp, s);
 }
@@ -299,9 +292,9 @@ void launch_particle_sort(const Geo& g, Parts<T> pp, PartSort<T> s, hipStream_t 
 // no longer be far below the smallest one's rounding), or are not finite,
 // takes float adds in the window (2^20 particles in a clump, masses over nine
 // decades: 295 us a step; with adds to the array 35500).  A particle
-// whose position is no number adds to the array.  FP64 keeps floating adds.  75 us a launch so; its waves wait most of
-// the time (65 %), on a particle's values and on the array's atomics at the
-// end: with the values loaded a turn ahead 55 us.
+// whose position is no number adds to the array.  FP64 keeps floating adds.  75 us a launch so, its waves
+// waiting for a particle's values and for the array's atomics at the end; 56 with
+// the values loaded a turn ahead (waiting 51 % of the time).
 template <class T>
 struct DepositCell {
   typedef T type;

@@ -9,7 +9,7 @@ collapse: the 1/r gas sphere on [-1, 1]^3 collapsing under its own gravity
 gravitational energies along the run, and radial profiles of density,
 pressure and radial velocity at the start and the end.  throughput: the
 turbulent-ISM box with self-gravity switched on: step time, the Poisson
-solve's share and its FFT passes' algorithmic bytes against HBM peak.
+solve's share and its passes' algorithmic bytes against HBM peak.
 Prints one JSON line.
 """
 from __future__ import annotations
@@ -125,11 +125,12 @@ def throughput(n, steps, warmup=2, G=1.0, precision=L.MHD_FP32):
                      "kernel_ms_per_launch": {k: v[0] / v[1] for k, v in prof.items() if v[1]}}
         sim.close()
     es = 4 if precision == L.MHD_FP32 else 8
-    N = n ** 3
-    # algorithmic bytes of one Poisson solve: density in, complex array out;
-    # six FFT passes and the k-space division each read and write the
-    # complex array; the gradient reads it and writes Psi and 3 components
-    byts = N * es + 2 * N * es + 6 * 2 * (2 * N * es) + 2 * (2 * N * es) + 2 * N * es + 4 * N * es
+    N, S = n ** 3, 2 * n * n * (n // 2 + 1)
+    # algorithmic bytes of one Poisson solve: density in and half spectrum out;
+    # y, z (forward, division, back) and y back each read and write the
+    # spectrum; it is read and Psi written; the gradient reads Psi and writes 3
+    # components
+    byts = es * (N + S + 3 * 2 * S + S + N + N + 3 * N)
     ms = out["self_gravity"]["kernel_ms_per_launch"]["gravity"]
     out["poisson_solve"] = {"ms": ms, "algorithmic_bytes": byts,
                             "achieved_GBps": byts / (ms * 1e-3) / 1e9,
