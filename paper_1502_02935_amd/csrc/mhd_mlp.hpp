@@ -263,15 +263,15 @@ __device__ __forceinline__ u32x2 act4(f32x4 d, const MlpLds& t) {
 // t (a barrier) before, and the reads of the outputs (wave_sync) after.
 //
 // 16x16x32 fragments halve the MFMAs (56 a wave) and the weight loads of
-// 16x16x16 ones: k_flux_mlp 199 -> 186 us a launch (128^3).  Weights and biases
-// are read again for every 16 samples: held through the loop (the compiler
+// 16x16x16 ones: k_flux_mlp 199 -> 186 us a launch (128^3, event timing).
+// Weights and biases are read again for every 16 samples: held through the loop (the compiler
 // hoists them if it may) they take 88 of the registers, and the kernel is bound
 // by what its waves overlap of its phases -- the stencil's reads (the address
 // unit 69 % busy), the table's LDS reads (77 %, two fifths of it bank
 // conflicts), the vector instructions (70 %).  With them reloaded and the
-// outputs in place of the inputs 5 waves a SIMD fit where 4 did: 186 -> 172 us a
-// launch (6 waves, weights from LDS in blocks of 512 or 640, two blocks of
-// samples a load: slower than 4 waves).
+// outputs in place of the inputs 5 waves a SIMD fit where 4 did: 176 -> 162 us a
+// launch, both in turn on one card (172 on another; 6 waves, weights from LDS in
+// blocks of 512 or 640, two blocks of samples a load: slower than 4 waves).
 constexpr int kMlpOutLd = kXs / 2;  // floats from one sample's outputs to the next's
 __device__ __forceinline__ const float* mlp_out(const unsigned short* X, int sample) {
   return (const float*)X + sample * kMlpOutLd;

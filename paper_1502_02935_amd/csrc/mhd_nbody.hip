@@ -284,17 +284,17 @@ void launch_particle_sort(const Geo& g, Parts<T> pp, PartSort<T> s, hipStream_t 
 // ---------------------------------------------------------------------------
 
 // The deposit's window in LDS.  FP32: 64-bit fixed point.  An LDS add of
-// floats takes about 190 cycles a wave whatever its addresses (the LDS was
-// busy 96 % of a 212 us launch for 2^22 particles), an integer add a tenth of
-// that.  The unit is 2^-50 of a bound on one particle's density, so the sum
+// floats occupies the LDS 111 cycles a wave whatever its addresses (74 % of a
+// 219 us launch for 2^22 particles), an integer add 8.5.  The unit is 2^-50 of a bound on one particle's density, so the sum
 // of a chunk's particles (at most kChunk = 2^11) stays below 2^62 and is exact
 // to that unit; a chunk whose masses differ by more than 2^20 (the unit would
 // no longer be far below the smallest one's rounding), or are not finite,
 // takes float adds in the window (2^20 particles in a clump, masses over nine
 // decades: 295 us a step; with adds to the array 35500).  A particle
-// whose position is no number adds to the array.  FP64 keeps floating adds.  75 us a launch so, its waves
-// waiting for a particle's values and for the array's atomics at the end; 56 with
-// the values loaded a turn ahead (waiting 51 % of the time).
+// whose position is no number adds to the array.  In fixed point a launch took
+// 75 us, its waves waiting for a particle's values and for the array's atomics at
+// the end; 56 with the values loaded a turn ahead (waiting 51 % of the time).
+// FP64 keeps floating adds.
 template <class T>
 struct DepositCell {
   typedef T type;
